@@ -426,7 +426,8 @@ int dpsnn_waves(dpsnn_net* net, const dpsnn_wave_params* wp, dpsnn_wave_result* 
  * y = m / grid_w), bin b of it is absolute bin bin0 + b of width bin_steps
  * steps of dt_ms.  stream: a hipStream_t, or NULL for the default stream;
  * wp->net and wp->n_bins are ignored.  Scratch from hipMalloc, freed before
- * returning. */
+ * returning (with counts past 65535 a table of 8 bytes per count among it;
+ * NOMEM for a count of 2^32 - 2 or more). */
 int dpsnn_waves_counts(const uint32_t* dev_counts, int64_t n_bins, int32_t grid_w,
                        int32_t grid_h, int32_t n_pops, int32_t bin_steps, double dt_ms,
                        int64_t bin0, const dpsnn_wave_params* wp, void* stream,

@@ -353,6 +353,12 @@ struct WaveArgs {
   int32_t* wave_n;
   double* grid;             // [batch][M] transition times of a wave batch
 };
+// Whether a table of log(i), i < lnt_n (lnt_n >= 2), serves windows whose
+// largest count is mx: the kernels read entries up to mx + 1, and mx + 2 may
+// pass 32 bits (a count of -1 or -2 in the caller's int32 tensor).
+__host__ __device__ inline bool lnt_covers(uint32_t lnt_n, uint32_t mx) {
+  return mx <= lnt_n - 2u;
+}
 constexpr int kWaveMaxBins = 4096;
 constexpr int kWaveMaxModules = 8192;
 constexpr int kWaveBatch = 256;  // waves per launch of the speed kernel

@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(256) k_wave_levels(WaveArgs a) {
   __shared__ unsigned long long s_sum[4];
   __shared__ uint32_t s_n[2][4];
   const uint32_t mx = *a.maxc;
-  if (mx + 2u > a.lnt_n) {  // past the table of logarithms: the host sees the maximum
+  if (!lnt_covers(a.lnt_n, mx)) {  // past the table of logarithms: the host sees the maximum
     if (tid == 0) a.cnt[m] = 0;
     return;
   }
