@@ -111,9 +111,13 @@ typedef struct dpsnn_params {
   int64_t spike_log_cap;               /* device spike-log entries; 0 = off */
   int64_t rate_bins_cap;               /* device rate bins kept [>= 1]      */
   int32_t queue_cap;                   /* half the entries of each tile's inbox
-                                          per step.  0 = default (4096, less
-                                          where (d_max + 5) x queue_cap entries
-                                          per tile would pass 16 GiB), -1 = no
+                                          per step; the lists of row pieces
+                                          that wait for their step take at most
+                                          as many bytes per tile and slot as
+                                          queue_cap entries.  0 = default (4096,
+                                          less where (d_max + 5) x queue_cap
+                                          entries per tile and the row offsets
+                                          would pass 16 GiB), -1 = no
                                           inboxes (every event is an atomic add
                                           into its slot), else 1 .. 2^20.
                                           Results do not depend on it.      */

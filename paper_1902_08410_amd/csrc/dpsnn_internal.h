@@ -18,7 +18,7 @@ constexpr int kDelayShift = 26;  // target word = target | delay index << 26
 constexpr int32_t kTargetMask = (1 << kDelayShift) - 1;
 constexpr int kMaxScanTiles = 14000;   // spike lists of kind 0: at most this many tiles
 constexpr int kQueueMaxSlots = 128;   // inboxes need D <= 128 slots
-constexpr int kQueueDefaultCap = 4096; // default queue_cap; a tile's inbox holds twice as many
+constexpr int kQueueDefaultCap = 4096; // default queue_cap; a tile's inbox holds twice as many entries
 constexpr int kInboxStride = 16;       // inbox counters 64 bytes apart
 constexpr int kDlvThreads = 512;       // threads of a delivery block
 constexpr int kPieceStride = 16;       // list counters 64 bytes apart
