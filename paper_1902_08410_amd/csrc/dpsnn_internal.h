@@ -22,6 +22,14 @@ constexpr int kQueueDefaultCap = 4096; // default queue_cap; a tile's inbox hold
 constexpr int kInboxStride = 16;       // inbox counters 64 bytes apart
 constexpr int kDlvThreads = 512;       // threads of a delivery block
 constexpr int kPieceStride = 16;       // list counters 64 bytes apart
+constexpr int kLongPiece = 64;        // most synapses of a piece (StepArgs::piece_len)
+constexpr int kShortPiece = 8;        // the same for rows of short segments, whose pieces
+                                      // share a wavefront's lanes
+// Rows of at most this many synapses per delay take short pieces.  48x48, us
+// of update and delivery per step, pieces of 64 and of 8: 5 synapses per delay
+// 36 + 151 and 36 + 63, 10: 30 + 79 and 32 + 49, 20: 28 + 50 and 29 + 42; 24:
+// 31 + 62 and 34 + 60, 50: 29 + 50 and 33 + 63.
+constexpr int kShortSegment = 20;
 constexpr int kPartShift = 4;        // a part of a step's list: at least 16 tiles of the delivery
 constexpr int kPartMax = 1024;         // order, and at most this many parts
 
@@ -202,6 +210,7 @@ struct StepArgs {
   // D) and part (2^part_shift places of the delivery order): piece_n may pass
   // piece_cap, the pieces past it were added into the slots
   int32_t n_parts, part_shift, piece_cap;
+  int32_t piece_len;       // most synapses of a piece: kLongPiece or kShortPiece
   uint32_t* piece_n;       // [D][n_parts * kPieceStride]
   unsigned long long* pieces;  // [D][n_parts][piece_cap]
   // spikes of the step, listed for plastic networks and handles without

@@ -866,15 +866,16 @@ __device__ __forceinline__ void row_to_slots(const StepArgs& a, int32_t s, const
 // Delivery of the events that arrive at step t + 1.  Rows are sorted by
 // (delay, target), so the events of a spike that arrive in one step are one
 // contiguous segment of its row.  When a neuron spikes, its segments are cut
-// into pieces of at most 64 synapses, and each piece is entered in the list
-// of its arrival step (push_pieces); a step reads the list that is due and
-// writes every event once, into the inbox its target tile sums in the next
-// step.  The list of a step is kept in parts by groups of tiles that are
+// into pieces of at most 64 synapses (8 where the segments are short), and
+// each piece is entered in the list of its arrival step (push_pieces); a step
+// reads the list that is due and writes every event once, into the inbox its
+// target tile sums in the next step.  The list of a step is kept in parts by groups of tiles that are
 // neighbours on the grid (delivery order), so consecutive pieces reach the
 // same tiles.
 //
 // A block takes slices of NW x R consecutive pieces, R per wavefront, one
-// lane per synapse, and sorts their events by target tile in LDS: the first
+// lane per synapse (short pieces: 64 per wavefront, their synapses one after
+// the other in R rows of lanes), and sorts their events by target tile in LDS: the first
 // lane of each run of one tile claims the tile's entry of a hash table and
 // adds the run there, which gives the run its rank; a prefix over the table
 // gives each tile's first position, and one returning atomic per distinct
@@ -884,8 +885,9 @@ __device__ __forceinline__ void row_to_slots(const StepArgs& a, int32_t s, const
 // Pieces per wavefront of the delivery kernel, and of its plastic form, whose
 // blocks share the CUs with those of the emission pass (24x24 plastic: 39 us
 // per step with 8, 45 with 16; 48x48 delivery 62 and 63 us, 96x96 126 and 116)
-// or with 8-byte entries, whose LDS would leave one block per CU; of the
-// fused and persistent schedules.
+// or with 8-byte entries, whose LDS would leave one block per CU, or with
+// short pieces (8 rows hold the synapses of 64); of the fused and persistent
+// schedules.
 constexpr int kDlvR = 16, kDlvRSmall = 8, kFusedR = 8, kPersistR = 8;
 // Table entries (bits): more than the distinct target tiles of a slice, which
 // grow with lambda (48x48: about 250 at lambda 1, over 1000 at 4; a table of
@@ -922,6 +924,7 @@ struct DeliverLds {
     struct {                    // before: heads of the runs of each piece, and
       uint8_t scr[BS / 64][R][68];    // inbox positions of runs outside the table
       uint32_t lone[BS / 64][64];
+      uint8_t own[BS / 64][64 * kShortPiece];  // piece of each synapse (short pieces)
     };
   };
   uint32_t wsum[BS / 64];
@@ -1054,14 +1057,15 @@ __device__ __forceinline__ int part_of(const Lds& L, int nparts, uint32_t s, uin
 
 // The pieces that are due in slot `slot` (the slot of step t + 1, whose
 // inboxes have parity `par`), shared among nb blocks of which this is b.
-template <typename Acc, int WDT, bool PACKED, int BS, int R, int HB, typename Lds>
+template <typename Acc, int WDT, bool PACKED, int BS, int R, int HB, bool SHORT, typename Lds>
 __device__ __forceinline__ void deliver_slices(const StepArgs& a, int slot, uint32_t par, int b,
                                                int nb, Lds& L) {
   typedef typename InboxEntry<Acc, WDT == DPSNN_W_F32 && !PACKED>::type Ent;
   constexpr int NW = BS / 64;
   constexpr int HN = 1 << HB;
   constexpr int PT = HN / BS;  // table entries per thread
-  static_assert(PT >= 1 && BS * R <= 65536 && R <= 64, "");
+  constexpr int WP = SHORT ? 64 : R;  // pieces of a wavefront in a slice
+  static_assert(PT >= 1 && BS * R <= 65536 && R <= 64 && (!SHORT || R == kShortPiece), "");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nparts = a.n_parts;
@@ -1069,13 +1073,15 @@ __device__ __forceinline__ void deliver_slices(const StepArgs& a, int slot, uint
   if (tid == 0) L.full = 0;
   const uint32_t S = part_prefix<BS>(a.piece_n + (int64_t)slot * nparts * kPieceStride, nparts,
                                      (uint32_t)a.piece_cap, L);
-  // every block takes `rounds` slices of P pieces: as few as a slice of NW R
+  // every block takes `rounds` slices of P pieces: as few as a slice of NW WP
   // pieces allows, all of one size, so that no block works on while the
-  // others have ended; never less than NW kMinR pieces, to share reservations
-  const uint32_t rounds = (S + (uint32_t)(nb * NW * R) - 1u) / (uint32_t)(nb * NW * R);
+  // others have ended; never less than NW WP / 4 pieces (long ones: NW kMinR),
+  // to share reservations
+  const uint32_t rounds = (S + (uint32_t)(nb * NW * WP) - 1u) / (uint32_t)(nb * NW * WP);
   if (rounds == 0) return;
+  constexpr uint32_t kMinP = NW * (SHORT ? WP / 4 : kMinR);
   uint32_t P = (S + (uint32_t)nb * rounds - 1u) / ((uint32_t)nb * rounds);
-  if (P < (uint32_t)(NW * kMinR)) P = (uint32_t)(NW * kMinR);
+  if (P < kMinP) P = kMinP;
   // consecutive blocks go to the eight XCDs in turn: those of one XCD take
   // consecutive pieces, so that the inboxes they share meet in its L2
   const int g = nb % 8 == 0 ? (b & 7) * (nb >> 3) + (b >> 3) : b;
@@ -1086,17 +1092,49 @@ __device__ __forceinline__ void deliver_slices(const StepArgs& a, int slot, uint
   const unsigned long long* pieces = a.pieces + (int64_t)slot * nparts * a.piece_cap;
   uint32_t* in_cnt = a.in_cnt + (int64_t)par * a.n_tiles * kInboxStride;
   Ent* in_q = static_cast<Ent*>(a.in_q) + (int64_t)par * a.n_tiles * a.in_stride;
-  // lane r holds piece r of the wavefront
+  // lane p holds piece p of the wavefront
   auto records = [&](uint32_t from) -> unsigned long long {
     const uint32_t k = (uint32_t)(lane * NW + wave), s = from + k;
-    if (lane >= R || k >= P || s >= s_end) return 0ull;
+    if (lane >= WP || k >= P || s >= s_end) return 0ull;
     uint32_t at;
     const int l = part_of(L, nparts, s, &at);
     return pieces[(int64_t)l * a.piece_cap + at];
   };
   int32_t tv[R];   // target words
   uint32_t cv[R];  // stored efficacies
+  int T = 0;       // events of the wavefront (SHORT)
   auto load = [&](unsigned long long rec) {
+    if constexpr (SHORT) {
+      // the pieces' synapses one after the other, 64 to a row: each finds its
+      // piece by its place in the wavefront's scratch
+      const uint32_t n = (uint32_t)rec >> 2 & 127u;
+      uint32_t incl = n;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t x = __shfl_up(incl, off);
+        if (lane >= off) incl += x;
+      }
+      T = __builtin_amdgcn_readlane((int)incl, 63);
+      for (uint32_t j = 0; j < n; ++j) L.own[wave][incl - n + j] = (uint8_t)lane;
+      wave_lds_sync();
+      const unsigned long long from = (rec >> 9) - (incl - n);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        tv[r] = 0;
+        cv[r] = 0;
+        if (r * 64 >= T) continue;  // uniform
+        // lanes past the last synapse read it
+        const int e = r * 64 + lane < T ? r * 64 + lane : T - 1;
+        const int p = L.own[wave][e];
+        const unsigned long long x =
+            ((unsigned long long)__shfl((uint32_t)(from >> 32), p) << 32 |
+             __shfl((uint32_t)from, p)) + (uint32_t)e;
+        tv[r] = load_target(a, (int64_t)x, 0u);
+        cv[r] = load_code<WDT>(a, (int64_t)x, 0u);
+        if (WDT == DPSNN_W_I8) cv[r] |= (__shfl((uint32_t)rec, p) & 3u) << 8;
+      }
+      return;
+    }
     const uint32_t rec_lo = (uint32_t)rec, rec_hi = (uint32_t)(rec >> 32);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -1116,13 +1154,16 @@ __device__ __forceinline__ void deliver_slices(const StepArgs& a, int slot, uint
     const bool more = s0 + P < s_end;
     load(rec);
     uint32_t rec_lo = (uint32_t)rec;
-    auto len = [&](int r) -> int { return (int)(__builtin_amdgcn_readlane(rec_lo, r) >> 2 & 127u); };
+    auto len = [&](int r) -> int {
+      if constexpr (SHORT) return T - 64 * r < 0 ? 0 : T - 64 * r < 64 ? T - 64 * r : 64;
+      return (int)(__builtin_amdgcn_readlane(rec_lo, r) >> 2 & 127u);
+    };
     Ent en[R];
     uint32_t tl[R];  // target tile
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       uint32_t c = cv[r];
-      if (WDT == DPSNN_W_I8) c |= (__builtin_amdgcn_readlane(rec_lo, r) & 3u) << 8;
+      if (WDT == DPSNN_W_I8 && !SHORT) c |= (__builtin_amdgcn_readlane(rec_lo, r) & 3u) << 8;
       en[r] = make_entry<Acc, WDT, PACKED>(a, c, (uint32_t)tv[r] & 1023u);
       tl[r] = (uint32_t)(tv[r] & kTargetMask) >> 10;
     }
@@ -1282,48 +1323,65 @@ __device__ __forceinline__ void deliver_slices(const StepArgs& a, int slot, uint
 // wavefront per piece (48x48 with a single delay, 16 pieces a spike, 7 % of the
 // neurons in the largest step: update 1341 us when lists held a piece per
 // neuron and the lane that found one full added its synapses alone, 64 now).
+//
+// Lanes take (delay, spike) pairs, delay first: the lanes of one delay follow
+// each other, so a prefix over the wavefront and one returning atomic per
+// delay give every pair its place (48x48: update 30.1 us with an atomic per
+// pair, 28.7 so; with 100 synapses a neuron and 96 Hz 70 and 36).
 template <typename Acc, int WDT>
 __device__ __forceinline__ void push_pieces(const StepArgs& a, int place, int now, int l0, int n,
                                             const int32_t* s_spk) {
-  const int nl = a.n_del - l0, lane = threadIdx.x & 63;
+  const int nl = a.n_del - l0, lane = threadIdx.x & 63, items = n * nl;
+  const int plen = a.piece_len;
   // (from the last wavefront on: the first ones deliver the events of delay 1
   // meanwhile in the fused schedule: 24x24 population model 16.9 -> 16.1 us)
-  for (int i0 = __builtin_amdgcn_readfirstlane((tile_tid() & 192) ^ 192); i0 < n * nl; i0 += 256) {
+  for (int i0 = __builtin_amdgcn_readfirstlane((tile_tid() & 192) ^ 192); i0 < items; i0 += 256) {
     const int i = i0 + lane;
-    int len = 0, slot = 0;
-    uint32_t pop = 0, lost = 0;
+    int len = 0, slot = 0, head = 0, tail = 0;
+    uint32_t pop = 0, np = 0, lost = 0;
     int64_t first = 0;
-    if (i < n * nl) {
-      const int k = i / nl, l = l0 + (i - k * nl);
-      const int32_t s = s_spk[k];
+    if (i < items) {
+      const int d = i / n, l = l0 + d;
+      const int32_t s = s_spk[i - d * n];
       const uint16_t* ro = a.row_off + (int64_t)s * (a.n_del + 1) + l;
       const int o0 = ro[0];
       len = (int)ro[1] - o0;
       slot = now + a.d_min + l;
       if (slot >= a.D) slot -= a.D;
       first = (int64_t)s * a.row_stride + o0;
-      if (len > 0) {
-        if (WDT == DPSNN_W_I8) {
-          int32_t ms;
-          int q;
-          module_pop(a, s, &ms, &q);
-          pop = (uint32_t)q;
-        }
-        const int64_t part = (int64_t)slot * a.n_parts + (place >> a.part_shift);
-        uint32_t at = atomicAdd(&a.piece_n[part * kPieceStride], (uint32_t)((len + 63) / 64));
-        int o = 0;
-        for (; o < len && at < (uint32_t)a.piece_cap; o += 64, ++at)
-          a.pieces[part * a.piece_cap + at] = piece_make(first + o, len - o < 64 ? len - o : 64, pop);
-        lost = o < len ? (uint32_t)(len - o) : 0u;
+      np = (uint32_t)(len + plen - 1) / (uint32_t)plen;
+      if (WDT == DPSNN_W_I8 && len > 0) {
+        int32_t ms;
+        int q;
+        module_pop(a, s, &ms, &q);
+        pop = (uint32_t)q;
       }
+      // first and last lane of the delay
+      head = d * n - i0 > 0 ? d * n - i0 : 0;
+      tail = (d + 1) * n - i0 < 64 ? (d + 1) * n - i0 - 1 : 63;
     }
+    uint32_t incl = np;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t x = __shfl_up(incl, off);
+      if (lane >= off) incl += x;
+    }
+    const uint32_t before = __shfl(incl - np, head), all = __shfl(incl, tail) - before;
+    const int64_t part = (int64_t)slot * a.n_parts + (place >> a.part_shift);
+    uint32_t at = 0;
+    if (i < items && lane == head && all) at = atomicAdd(&a.piece_n[part * kPieceStride], all);
+    at = __shfl(at, head) + incl - np - before;
+    int o = 0;
+    for (; o < len && at < (uint32_t)a.piece_cap; o += plen, ++at)
+      a.pieces[part * a.piece_cap + at] = piece_make(first + o, len - o < plen ? len - o : plen, pop);
+    lost = o < len ? (uint32_t)(len - o) : 0u;
     for (unsigned long long over = __ballot(lost > 0); over; over &= over - 1) {
       const int from = __ffsll(over) - 1;
       const int m = __shfl((int)lost, from), to = __shfl(slot, from);
       const int64_t x = __shfl((long long)(first + len - (int)lost), from);
       const uint32_t q = __shfl(pop, from);
-      for (int o = 0; o < m; o += 64)
-        piece_to_slot<Acc, WDT>(a, piece_make(x + o, m - o < 64 ? m - o : 64, q), to, lane);
+      for (int p = 0; p < m; p += 64)
+        piece_to_slot<Acc, WDT>(a, piece_make(x + p, m - p < 64 ? m - p : 64, q), to, lane);
     }
   }
 }
@@ -1482,10 +1540,11 @@ __device__ __forceinline__ void clear_counters(const StepArgs& a, const StepTime
       a.emit_n[(((T.t + 1u) & 1u) * (uint32_t)a.n_parts + (uint32_t)c) * kPieceStride] = 0u;
 }
 
-template <typename Acc, int WDT, bool PLAST, bool PACKED>
-__global__ void __launch_bounds__(kDlvThreads, PLAST ? 6 : 4) k_deliver(StepArgs a, StepOff o) {
+template <typename Acc, int WDT, bool PLAST, bool PACKED, bool SHORT>
+__global__ void __launch_bounds__(kDlvThreads, PLAST || SHORT ? 6 : 4)
+    k_deliver(StepArgs a, StepOff o) {
   typedef typename InboxEntry<Acc, WDT == DPSNN_W_F32 && !PACKED>::type Ent;
-  constexpr int R = PLAST || sizeof(Ent) == 8 ? kDlvRSmall : kDlvR;
+  constexpr int R = PLAST || SHORT || sizeof(Ent) == 8 ? kDlvRSmall : kDlvR;
   __shared__ DeliverLds<Ent, kDlvThreads, R, kDlvHash> L;
   const StepTime T = step_time(a, o);
   if ((int)blockIdx.x < a.log_blocks) {
@@ -1502,7 +1561,8 @@ __global__ void __launch_bounds__(kDlvThreads, PLAST ? 6 : 4) k_deliver(StepArgs
   const int nb = a.deliver_grid;
   const int next = (int)T.slot + 1 < a.D ? (int)T.slot + 1 : 0;
   if (a.q_cap)
-    deliver_slices<Acc, WDT, PACKED, kDlvThreads, R, kDlvHash>(a, next, (T.t + 1u) & 1u, b, nb, L);
+    deliver_slices<Acc, WDT, PACKED, kDlvThreads, R, kDlvHash, SHORT>(a, next, (T.t + 1u) & 1u, b,
+                                                                     nb, L);
 }
 
 // The events that arrive one step after the spikes s_spk[0 .. n) (d_min = 1:
@@ -1561,7 +1621,7 @@ __device__ __forceinline__ void deliver_first(const StepArgs& a, const StepTime&
 // of its last), the next n_dlv deliver the pieces that are due at t + 1, all
 // of them emitted before this step; the others update two tiles each, list
 // their spikes for later steps and deliver their events of delay 1 themselves.
-template <typename Acc, int WDT, int NP, int FMT>
+template <typename Acc, int WDT, int NP, int FMT, bool SHORT>
 __global__ void __launch_bounds__(kDlvThreads, 6) k_step(StepArgs a, StepOff o, int n_dlv) {
   constexpr bool PACKED = FMT == kFmtPacked;
   __shared__ union {
@@ -1583,7 +1643,7 @@ __global__ void __launch_bounds__(kDlvThreads, 6) k_step(StepArgs a, StepOff o, 
   b -= a.log_blocks;
   if (b < n_dlv) {
     if (a.q_cap)
-      deliver_slices<Acc, WDT, PACKED, kDlvThreads, kFusedR, kFusedHash>(
+      deliver_slices<Acc, WDT, PACKED, kDlvThreads, kFusedR, kFusedHash, SHORT>(
           a, next, (T.t + 1u) & 1u, b, n_dlv, L.d);
     return;
   }
@@ -1654,8 +1714,11 @@ __global__ void __launch_bounds__(256) k_persist(StepArgs a, StepOff o, uint32_t
     if (!a.q_cap)
       emission_items<Acc, WDT, false, 256>(a, T, (int)blockIdx.x, G, L.d);
     const int next = (int)T.slot + 1 < a.D ? (int)T.slot + 1 : 0;
-    if (a.q_cap)
-      deliver_slices<Acc, WDT, FMT == kFmtPacked, 256, kPersistR, kPersistHash>(
+    if (a.q_cap && a.piece_len == kShortPiece)
+      deliver_slices<Acc, WDT, FMT == kFmtPacked, 256, kShortPiece, kPersistHash, true>(
+          a, next, (T.t + 1u) & 1u, (int)blockIdx.x, G, L.d);
+    else if (a.q_cap)
+      deliver_slices<Acc, WDT, FMT == kFmtPacked, 256, kPersistR, kPersistHash, false>(
           a, next, (T.t + 1u) & 1u, (int)blockIdx.x, G, L.d);
     grid.sync();
   }
@@ -1813,24 +1876,33 @@ static void launch_neuron(const StepArgs& a, uint32_t t_off, hipStream_t st) {
   launch_neuron_fmt<Acc, kFmtWide, DPSNN_W_F32>(a, t_off, st);
 }
 
-template <typename Acc>
-static void launch_deliver(const StepArgs& a, int wdt, uint32_t t_off, hipStream_t st) {
+template <typename Acc, bool SHORT>
+static void launch_deliver_len(const StepArgs& a, int wdt, uint32_t t_off, hipStream_t st) {
   const dim3 block(kDlvThreads);
   const dim3 grid((unsigned)(a.log_blocks + a.emit_blocks + (a.q_cap ? a.deliver_grid : 0)));
   const StepOff o = step_off(a, t_off);
   const bool packed = sizeof(Acc) == 4 && a.q_packed;
+  constexpr bool P4 = sizeof(Acc) == 4;
   if (a.plastic && packed)
-    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_F32, true, sizeof(Acc) == 4>), grid, block, 0, st, a, o);
+    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_F32, true, P4, SHORT>), grid, block, 0, st, a, o);
   else if (a.plastic)
-    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_F32, true, false>), grid, block, 0, st, a, o);
+    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_F32, true, false, SHORT>), grid, block, 0, st, a, o);
   else if (wdt == DPSNN_W_F32 && packed)
-    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_F32, false, sizeof(Acc) == 4>), grid, block, 0, st, a, o);
+    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_F32, false, P4, SHORT>), grid, block, 0, st, a, o);
   else if (wdt == DPSNN_W_F32)
-    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_F32, false, false>), grid, block, 0, st, a, o);
+    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_F32, false, false, SHORT>), grid, block, 0, st, a, o);
   else if (wdt == DPSNN_W_F16)
-    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_F16, false, false>), grid, block, 0, st, a, o);
+    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_F16, false, false, SHORT>), grid, block, 0, st, a, o);
   else
-    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_I8, false, false>), grid, block, 0, st, a, o);
+    hipLaunchKernelGGL((k_deliver<Acc, DPSNN_W_I8, false, false, SHORT>), grid, block, 0, st, a, o);
+}
+
+template <typename Acc>
+static void launch_deliver(const StepArgs& a, int wdt, uint32_t t_off, hipStream_t st) {
+  if (a.piece_len == kShortPiece)
+    launch_deliver_len<Acc, true>(a, wdt, t_off, st);
+  else
+    launch_deliver_len<Acc, false>(a, wdt, t_off, st);
 }
 
 template <typename Acc>
@@ -1839,26 +1911,35 @@ static void launch_split(const StepArgs& a, int wdt, uint32_t t_off, hipStream_t
   launch_deliver<Acc>(a, wdt, t_off, st);
 }
 
-template <typename Acc, int NP>
-static void launch_fused_np(const StepArgs& a, int wdt, uint32_t t_off, hipStream_t st) {
+template <typename Acc, int NP, bool SHORT>
+static void launch_fused_len(const StepArgs& a, int wdt, uint32_t t_off, hipStream_t st) {
   const int nd = a.fused_dlv;
-  const dim3 tiles((unsigned)(a.log_blocks + nd + (a.n_tiles + 1) / 2)), block(kDlvThreads);
+  const dim3 grid((unsigned)(a.log_blocks + nd + (a.n_tiles + 1) / 2)), block(kDlvThreads);
   const StepOff o = step_off(a, t_off);
   if (wdt == DPSNN_W_F16) {
-    hipLaunchKernelGGL((k_step<Acc, DPSNN_W_F16, NP, kFmtCode>), tiles, block, 0, st, a, o, nd);
+    hipLaunchKernelGGL((k_step<Acc, DPSNN_W_F16, NP, kFmtCode, SHORT>), grid, block, 0, st, a, o, nd);
     return;
   }
   if (wdt == DPSNN_W_I8) {
-    hipLaunchKernelGGL((k_step<Acc, DPSNN_W_I8, NP, kFmtCode>), tiles, block, 0, st, a, o, nd);
+    hipLaunchKernelGGL((k_step<Acc, DPSNN_W_I8, NP, kFmtCode, SHORT>), grid, block, 0, st, a, o, nd);
     return;
   }
   if constexpr (sizeof(Acc) == 4) {
     if (a.q_packed) {
-      hipLaunchKernelGGL((k_step<Acc, DPSNN_W_F32, NP, kFmtPacked>), tiles, block, 0, st, a, o, nd);
+      hipLaunchKernelGGL((k_step<Acc, DPSNN_W_F32, NP, kFmtPacked, SHORT>), grid, block, 0, st, a, o,
+                         nd);
       return;
     }
   }
-  hipLaunchKernelGGL((k_step<Acc, DPSNN_W_F32, NP, kFmtWide>), tiles, block, 0, st, a, o, nd);
+  hipLaunchKernelGGL((k_step<Acc, DPSNN_W_F32, NP, kFmtWide, SHORT>), grid, block, 0, st, a, o, nd);
+}
+
+template <typename Acc, int NP>
+static void launch_fused_np(const StepArgs& a, int wdt, uint32_t t_off, hipStream_t st) {
+  if (a.piece_len == kShortPiece)
+    launch_fused_len<Acc, NP, true>(a, wdt, t_off, st);
+  else
+    launch_fused_len<Acc, NP, false>(a, wdt, t_off, st);
 }
 
 template <typename Acc>
