@@ -837,11 +837,13 @@ __device__ __forceinline__ Acc fix_of(const StepArgs& a, uint32_t code, const Co
     return dec(code << kCodeShift);
 }
 
-// Handles without inboxes: every event of a spike of this step is added into
-// the slot of its arrival (one wavefront per row).
+// Handles without inboxes: the events of synapses p0 .. p0 + 255 of the row of
+// a spike of this step are added into the slots of their arrival, by one
+// wavefront, all loads before the first addition (a row at a time, load by
+// load: 2x2 modules 19.4 us per step in the split schedule, 11.3 so).
 template <typename Acc, int WDT>
-__device__ __forceinline__ void row_to_slots(const StepArgs& a, int32_t s, const StepTime& T,
-                                             int lane) {
+__device__ __forceinline__ void row_to_slots(const StepArgs& a, int32_t s, int p0,
+                                             const StepTime& T, int lane) {
   const CodeDec<Acc> dec = code_dec<Acc>(a, s >> 10);
   uint32_t pop = 0;
   if (WDT == DPSNN_W_I8) {
@@ -854,12 +856,21 @@ __device__ __forceinline__ void row_to_slots(const StepArgs& a, int32_t s, const
   int slot0 = (int)T.slot + a.d_min;  // slot of arrival at t + d_min
   if (slot0 >= a.D) slot0 -= a.D;
   const int64_t rb = (int64_t)s * a.row_stride;
-  for (int p = lane; p < a.K_out; p += 64) {
-    const int32_t tv = a.tgt[rb + p];
-    int sl = slot0 + (int)((uint32_t)tv >> kDelayShift);
+  int32_t tv[4];
+  uint32_t cv[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {  // (lanes past the row read its last synapse)
+    const int p = p0 + 64 * u + lane < a.K_out ? p0 + 64 * u + lane : a.K_out - 1;
+    tv[u] = load_target(a, rb, (uint32_t)p);
+    cv[u] = load_code<WDT>(a, rb, (uint32_t)p);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (p0 + 64 * u + lane >= a.K_out) continue;
+    int sl = slot0 + (int)((uint32_t)tv[u] >> kDelayShift);
     if (sl >= a.D) sl -= a.D;
-    atomic_add_fix<Acc>(slots + (int64_t)sl * a.N_pad + (tv & kTargetMask),
-                        fix_of<Acc, WDT>(a, load_code<WDT>(a, rb, (uint32_t)p) | pop, dec));
+    atomic_add_fix<Acc>(slots + (int64_t)sl * a.N_pad + (tv[u] & kTargetMask),
+                        fix_of<Acc, WDT>(a, cv[u] | pop, dec));
   }
 }
 
@@ -1387,9 +1398,9 @@ __device__ __forceinline__ void push_pieces(const StepArgs& a, int place, int no
 }
 
 // Work done when a spike is emitted (plastic networks: the activations of
-// its synapses, one wavefront per 256; handles without inboxes: its events
-// into the slots, one wavefront per row), for the listed spikes of this step:
-// wavefront w of nw takes items w, w + nw, ...
+// its synapses; handles without inboxes: its events into the slots), for the
+// listed spikes of this step, one wavefront per 256 synapses: wavefront w of
+// nw takes items w, w + nw, ...
 template <typename Acc, int WDT, bool PLAST, int BS, typename Lds>
 __device__ __forceinline__ void emission_items(const StepArgs& a, const StepTime& T, int b, int nb,
                                                Lds& L) {
@@ -1397,17 +1408,18 @@ __device__ __forceinline__ void emission_items(const StepArgs& a, const StepTime
   const uint32_t n = part_prefix<BS>(a.emit_n + (T.t & 1u) * (uint32_t)(a.n_parts * kPieceStride),
                                      a.n_parts, ~0u, L);
   lds_barrier();
-  const int cpr = PLAST ? (a.K_out + 255) / 256 : 1;
-  const int64_t items = (int64_t)n * cpr;
-  for (int64_t it = (int64_t)b * (BS / 64) + (threadIdx.x >> 6); it < items;
-       it += (int64_t)nb * (BS / 64)) {
-    const uint32_t k = (uint32_t)(it / cpr);
+  const uint32_t cpr = (uint32_t)(a.K_out + 255) / 256u;  // at most 16, of 2^26 spikes
+  const uint32_t items = n * cpr;
+  for (uint32_t it = __builtin_amdgcn_readfirstlane(b * (BS / 64) + (int)(threadIdx.x >> 6));
+       it < items; it += (uint32_t)(nb * (BS / 64))) {
+    const uint32_t k = it / cpr;
     uint32_t at;
     const int part = part_of(L, a.n_parts, k, &at);
     const int32_t s = __builtin_amdgcn_readfirstlane(
         a.emit_id[((int64_t)part << (a.part_shift + 10)) + at]);
-    if (PLAST) row_plasticity(a, s, (int)(it - (int64_t)k * cpr) * 256, T.t, lane);
-    if (!a.q_cap && it == (int64_t)k * cpr) row_to_slots<Acc, WDT>(a, s, T, lane);
+    const int p0 = (int)(it - k * cpr) * 256;
+    if (PLAST) row_plasticity(a, s, p0, T.t, lane);
+    if (!a.q_cap) row_to_slots<Acc, WDT>(a, s, p0, T, lane);
   }
 }
 
@@ -1664,8 +1676,10 @@ __global__ void __launch_bounds__(kDlvThreads, 6) k_step(StepArgs a, StepOff o, 
     push_pieces<Acc, WDT>(a, a.tile_place[tile], (int)T.slot, a.d_min == 1 ? 1 : 0, n, spk);
     if (a.d_min == 1) deliver_first<Acc, WDT, PACKED>(a, T, n, spk);
   } else {
-    for (int k = tid >> 6; k < n; k += 4)
-      row_to_slots<Acc, WDT>(a, __builtin_amdgcn_readfirstlane(spk[k]), T, tid & 63);
+    for (int k = tid >> 6; k < n; k += 4) {
+      const int32_t id = __builtin_amdgcn_readfirstlane(spk[k]);
+      for (int p0 = 0; p0 < a.K_out; p0 += 256) row_to_slots<Acc, WDT>(a, id, p0, T, tid & 63);
+    }
   }
 }
 
