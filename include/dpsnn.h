@@ -61,7 +61,10 @@ extern "C" {
 /* Step schedules (results are bit-identical; only speed differs). */
 #define DPSNN_SCHED_FUSED 0 /* one kernel per step: some blocks deliver the
                                events that are due while the others update
-                               (networks below 1.2 M neurons) */
+                               (the default below 1.2 M neurons, 0.5 M for
+                               at most 8 synapses per delay, unless K_out is
+                               more than 64 per delay from d_min = 1, or 256
+                               without inboxes) */
 #define DPSNN_SCHED_SPLIT 1 /* neuron kernel, then a delivery kernel that
                                spreads the due events over the whole GPU */
 #define DPSNN_SCHED_PERSIST 2 /* the split schedule's work for many steps in
