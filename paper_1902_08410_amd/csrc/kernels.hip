@@ -1757,10 +1757,12 @@ __global__ void __launch_bounds__(256) k_tick(StepArgs a, uint32_t n, int log_la
     for (int c = threadIdx.x; c < 2 * a.n_parts; c += 256) a.emit_n[c * kPieceStride] = 0u;
 }
 
-// Folds the events that are still to arrive after t steps into the slots:
-// the inboxes (arriving at t) and the lists of the later steps; all are left
-// empty and every slot marked.  Block b takes tile b and the parts b, b +
-// gridDim.x, ... of the lists.
+// Folds the events that are still to arrive after t steps into the slots: the
+// inboxes (arriving at t) and the lists of the later steps; all are left empty
+// and the slots that got something marked.  Block b < n_tiles takes the inbox
+// of tile b, the others a list each, `share` of them one list (2x2 modules
+// with an efficacy update every 10 steps: 26.1 us per step when the tiles'
+// blocks took the lists too and marked every slot, 18.3 so).
 template <typename Acc, typename E>
 __device__ __forceinline__ void drain_inbox(const StepArgs& a, int tile, uint32_t t,
                                             const CodeDec<Acc>& dec) {
@@ -1772,31 +1774,43 @@ __device__ __forceinline__ void drain_inbox(const StepArgs& a, int tile, uint32_
             (int64_t)tile * 1024;
   for (uint32_t e = threadIdx.x; e < n_in; e += blockDim.x)
     atomic_add_fix<Acc>(sl + (ent_x(iq[e]) & 1023u), ent_w<Acc>(iq[e], dec));
+  __syncthreads();  // every thread has read the count
+  if (threadIdx.x == 0 && got) {
+    a.in_cnt[box * kInboxStride] = 0;
+    a.s_dirty[(int64_t)tile * a.D + t % (uint32_t)a.D] = 1u;
+  }
 }
 
 template <typename Acc, int WDT>
-__global__ void __launch_bounds__(256) k_drain(StepArgs a, uint32_t t) {
-  const int tile = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const CodeDec<Acc> dec = code_dec<Acc>(a, tile);
-  if (a.q_code)
-    drain_inbox<Acc, CodeEntry>(a, tile, t, dec);
-  else if (sizeof(Acc) == 4 && a.q_packed)
-    drain_inbox<Acc, PackedEntry>(a, tile, t, dec);
-  else
-    drain_inbox<Acc, QEntry<Acc>>(a, tile, t, dec);
-  const int now = (int)(t % (uint32_t)a.D);  // the list of t is delivered already
-  for (int x = tile; x < a.D * a.n_parts; x += (int)gridDim.x) {
-    const int slot = x / a.n_parts;
-    const uint32_t got = a.piece_n[(int64_t)x * kPieceStride];
-    const uint32_t n = slot == now ? 0u : got < (uint32_t)a.piece_cap ? got : (uint32_t)a.piece_cap;
-    const unsigned long long* p = a.pieces + (int64_t)x * a.piece_cap;
-    for (uint32_t k = wave; k < n; k += 4) piece_to_slot<Acc, WDT>(a, p[k], slot, lane);
-    __syncthreads();
-    if (threadIdx.x == 0) a.piece_n[(int64_t)x * kPieceStride] = 0;
+__global__ void __launch_bounds__(256) k_drain(StepArgs a, uint32_t t, int share) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if ((int)blockIdx.x < a.n_tiles) {
+    const int tile = (int)blockIdx.x;
+    const CodeDec<Acc> dec = code_dec<Acc>(a, tile);
+    if (a.q_code)
+      drain_inbox<Acc, CodeEntry>(a, tile, t, dec);
+    else if (sizeof(Acc) == 4 && a.q_packed)
+      drain_inbox<Acc, PackedEntry>(a, tile, t, dec);
+    else
+      drain_inbox<Acc, QEntry<Acc>>(a, tile, t, dec);
+    return;
   }
-  __syncthreads();
-  if (threadIdx.x == 0) a.in_cnt[((int64_t)(t & 1u) * a.n_tiles + tile) * kInboxStride] = 0;
-  for (int k = threadIdx.x; k < a.D; k += blockDim.x) a.s_dirty[(int64_t)tile * a.D + k] = 1u;
+  const int now = (int)(t % (uint32_t)a.D);  // the list of t is delivered already
+  const int y = (int)blockIdx.x - a.n_tiles, x = y / share;
+  const int slot = x / a.n_parts;
+  uint32_t* cnt = a.piece_n + (int64_t)x * kPieceStride;
+  const uint32_t got = cnt[0];
+  const uint32_t n = slot == now ? 0u : got < (uint32_t)a.piece_cap ? got : (uint32_t)a.piece_cap;
+  const unsigned long long* p = a.pieces + (int64_t)x * a.piece_cap;
+  for (uint32_t k = (uint32_t)((y - x * share) * 4 + wave); k < n; k += (uint32_t)(4 * share))
+    piece_to_slot<Acc, WDT>(a, p[k], slot, lane);
+  __syncthreads();  // every thread has read the count
+  // the last of the list's blocks empties it (the word after the count, which
+  // nothing else uses, tells them apart)
+  if (threadIdx.x == 0 && (share == 1 || atomicAdd(cnt + 1, 1u) == (uint32_t)share - 1u)) {
+    cnt[0] = 0;
+    cnt[1] = 0;
+  }
 }
 
 // ------------------------------------------------------------------------
@@ -2043,21 +2057,22 @@ size_t deliver_lds_bytes() { return sizeof(DeliverLds<uint32_t, kDlvThreads, kDl
 
 hipError_t launch_drain(const StepArgs& a, int wdt, int acc_bits, uint32_t t, hipStream_t st) {
   if (a.q_cap == 0 || a.n_tiles == 0) return hipSuccess;
-  const dim3 grid((unsigned)a.n_tiles), block(256);
+  const int lists = a.D * a.n_parts, share = std::max(1, std::min(16, 1024 / lists));
+  const dim3 grid((unsigned)(a.n_tiles + lists * share)), block(256);
   if (acc_bits == 32) {
     if (wdt == DPSNN_W_F32)
-      hipLaunchKernelGGL((k_drain<int32_t, DPSNN_W_F32>), grid, block, 0, st, a, t);
+      hipLaunchKernelGGL((k_drain<int32_t, DPSNN_W_F32>), grid, block, 0, st, a, t, share);
     else if (wdt == DPSNN_W_F16)
-      hipLaunchKernelGGL((k_drain<int32_t, DPSNN_W_F16>), grid, block, 0, st, a, t);
+      hipLaunchKernelGGL((k_drain<int32_t, DPSNN_W_F16>), grid, block, 0, st, a, t, share);
     else
-      hipLaunchKernelGGL((k_drain<int32_t, DPSNN_W_I8>), grid, block, 0, st, a, t);
+      hipLaunchKernelGGL((k_drain<int32_t, DPSNN_W_I8>), grid, block, 0, st, a, t, share);
   } else {
     if (wdt == DPSNN_W_F32)
-      hipLaunchKernelGGL((k_drain<int64_t, DPSNN_W_F32>), grid, block, 0, st, a, t);
+      hipLaunchKernelGGL((k_drain<int64_t, DPSNN_W_F32>), grid, block, 0, st, a, t, share);
     else if (wdt == DPSNN_W_F16)
-      hipLaunchKernelGGL((k_drain<int64_t, DPSNN_W_F16>), grid, block, 0, st, a, t);
+      hipLaunchKernelGGL((k_drain<int64_t, DPSNN_W_F16>), grid, block, 0, st, a, t, share);
     else
-      hipLaunchKernelGGL((k_drain<int64_t, DPSNN_W_I8>), grid, block, 0, st, a, t);
+      hipLaunchKernelGGL((k_drain<int64_t, DPSNN_W_I8>), grid, block, 0, st, a, t, share);
   }
   return hipGetLastError();
 }
