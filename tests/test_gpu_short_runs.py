@@ -1,0 +1,61 @@
+"""Runs of a few steps launched directly: the counter and the log advance once a
+run, so that a step costs what it costs in a longer run."""
+import time
+
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_1902_08410_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def L():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1902_08410_amd import dpsnn
+    dpsnn.lib()
+    return dpsnn
+
+
+@pytest.mark.parametrize("sched", [0, 1, 2])
+def test_runs_of_any_length_log_every_step(L, sched):
+    p = W.tiny(w=3, h=2, K=400, K_out=120, nu_ext_hz=[3500.0, 3500.0], spike_log_cap=1 << 18,
+               rate_bins_cap=64)
+    print("[case] short runs, schedule", sched, flush=True)
+    net, orc = L.dpsnn_build(p, 9), O.Oracle(p, 9, store_rows=True)
+    L.dpsnn_set_schedule(net, sched)
+    got = []
+    for n in (1, 2, 1, 5, 15, 16, 17, 1, 10, 3, 29, 1):
+        L.dpsnn_step(net, n)
+        orc.step(n)
+        if n != 5:  # some runs follow each other with the log unread
+            got.append(L.dpsnn_read_spikes(net))
+    st, ids = (np.concatenate(x) for x in zip(*got))
+    ost, oids = orc.spikes()
+    assert len(st) > 100 and np.array_equal(st, ost) and np.array_equal(ids, oids)
+    assert L.dpsnn_stats(net)["n_spikes"] == len(st)
+    net.close()
+
+
+def test_a_step_of_a_short_run_costs_no_more(L):
+    """5000 neurons on the default stream, nothing read between: runs of 15
+    steps against runs of 20 (1.43 times the time per step with a counter
+    launch after each step of the shorter ones)."""
+    net = L.dpsnn_build(W.swa(rate_bins_cap=1 << 14), 5)
+    L.dpsnn_step(net, 300)
+    us = {}
+    for _ in range(3):
+        for n in (15, 20):
+            L.dpsnn_sync(net)
+            t = time.perf_counter()
+            for _ in range(60):
+                L.dpsnn_step(net, n)
+            L.dpsnn_sync(net)
+            us[n] = min(us.get(n, 1e9), (time.perf_counter() - t) / (60 * n) * 1e6)
+    print("[case] us per step", us, flush=True)
+    net.close()
+    assert us[15] < 1.2 * us[20]
