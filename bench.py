@@ -359,6 +359,16 @@ def _net_spikes(dpsnn, h, n_nets):
     return [int(dpsnn.dpsnn_read_rates_net(h, k).sum()) for k in range(n_nets)]
 
 
+def own_grid(h, args) -> bool:
+    """Whether a handle delivers with the library's own grid: the statistics then
+    hold one block per tile, between 256 and 1024 (the autotuner tries that number
+    as the library's own grid only)."""
+    st = h.stats()
+    if not args.autotune and args.delivery and int(args.delivery.split(":")[1]):
+        return False
+    return st["deliver_blocks"] == min(1024, max(256, -(-st["n_index"] // 1024)))
+
+
 def time_group(nets, dpsnn, torch, stream, args, steps, S):
     """The timing protocol, the same for every group: warm-up bench steps,
     autotune, the timed bench steps (graph replay on a non-default stream,
@@ -519,14 +529,15 @@ def group_record(workload, wdt, nets, res, steps, S, args):
                         "bytes_per_synapse": h.stats()["bytes_total"] /
                         max(1, h.stats()["n_synapses"]),
                         "schedule": {0: "fused", 1: "split", 2: "persistent"}[res["sched"][k]],
-                        "deliver_blocks": h.stats()["deliver_blocks"],
-                        "spike_lists": {0: "per tile", 1: "appended",
-                                        2: "appended, merged reservations"}[
-                            h.stats()["spike_lists"]],
+                        "deliver_blocks": "the library's own" if own_grid(h, args)
+                        else h.stats()["deliver_blocks"],
+                        # kept and reported by the library, without effect
+                        "spike_lists": h.stats()["spike_lists"],
                         # the same launches without the autotuner: --autotune 0 --delivery
                         "delivery": "{}:{}:{}".format(
                             {0: "fused", 1: "split", 2: "split"}[res["sched"][k]],
-                            h.stats()["deliver_blocks"], h.stats()["spike_lists"])}
+                            0 if own_grid(h, args) else h.stats()["deliver_blocks"],
+                            h.stats()["spike_lists"])}
                     for k, (h, _, labels) in nets.items()},
         "gpu_ms_timed": res["gpu_ms"],
     }
@@ -710,8 +721,9 @@ def main():
                     help="steps per captured HIP graph (0: direct launches, as profiler "
                          "counter passes need); default: the library's")
     ap.add_argument("--delivery", default=None, metavar="SCHED:BLOCKS:LISTS",
-                    help="with --autotune 0: schedule (split or fused), delivery blocks "
-                         "and spike-list kind of every handle, e.g. split:1024:2")
+                    help="with --autotune 0: schedule (split or fused), delivery blocks (0: "
+                         "the library's own) and spike-list kind of every handle, e.g. "
+                         "split:0:2")
     ap.add_argument("--calibrate", action="store_true",
                     help="only copy 256 MiB device-to-device three times (counter calibration)")
     ap.add_argument("--summarize-rocprof", nargs=7, metavar=("KT", "FETCH", "WRITE", "CAL_FETCH",

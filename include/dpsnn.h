@@ -254,12 +254,12 @@ int dpsnn_step(dpsnn_net* net, int64_t n_steps);
 int dpsnn_set_schedule(dpsnn_net* net, int32_t sched);
 
 /* The split schedule's delivery: grid of the delivery kernel (blocks > 0;
- * 0 keeps the current one).  The reported default, one block per tile between
- * 256 and 1024, stands for the library's own grid: the blocks that are
- * resident at once.  spike_lists (0, for at most 14000 tiles, 1 or 2; -1
- * keeps the current kind) is kept and reported; the spikes of a step are
- * listed in one way whatever it is.  Results do not depend on either.
- * INVAL otherwise. */
+ * 0 keeps the current one).  Until a grid is set the library takes its own,
+ * as many blocks as are resident at once; deliver_blocks of the statistics
+ * then holds one block per tile, between 256 and 1024.  spike_lists (0, for
+ * at most 14000 tiles, 1 or 2; -1 keeps the current kind) is kept and
+ * reported; the spikes of a step are listed in one way whatever it is.
+ * Results do not depend on either.  INVAL otherwise. */
 int dpsnn_set_delivery(dpsnn_net* net, int32_t deliver_blocks, int32_t spike_lists);
 
 /* Kept for callers that set a routing grid: 1 .. number of 1024-neuron tiles,
@@ -275,13 +275,14 @@ int dpsnn_set_graph_steps(dpsnn_net* net, int64_t steps);
 
 /*
  * Time real steps with each available schedule, and for the split schedule
- * with several grid sizes of the delivery kernel and every spike-list kind
- * (they advance the simulation; results do not depend on any of them), and
- * keep the fastest.  Steps run in runs of K (the graph length when graphs
- * are in use, else min(probe_steps, 128)): one untimed run per candidate,
- * then max(1, probe_steps / K) rounds of one timed run per candidate, so
- * that every candidate sees the same mix of activity.  *chosen (may be
- * NULL) receives the schedule.  Synchronises.
+ * with several grid sizes of the delivery kernel (the library's own among
+ * them, reported as before dpsnn_set_delivery) and every spike-list kind (they
+ * advance the simulation; results do not depend on any of them), and keep the
+ * fastest schedule and grid; the kind stays as it is.  Steps run in runs of K
+ * (the graph length when graphs are in use, else min(probe_steps, 128)): one
+ * untimed run per candidate, then max(1, probe_steps / K) rounds of one timed
+ * run per candidate, so that every candidate sees the same mix of activity.
+ * *chosen (may be NULL) receives the schedule.  Synchronises.
  */
 int dpsnn_autotune(dpsnn_net* net, int64_t probe_steps, int32_t* chosen);
 
