@@ -316,8 +316,8 @@ hipError_t launch_phase(const StepArgs& a, int wdt, int acc_bits, int phase, uin
 // Fold every pending event into its slot and empty inboxes and lists; t is
 // the number of steps taken.
 hipError_t launch_drain(const StepArgs& a, int wdt, int acc_bits, uint32_t t, hipStream_t s);
-// LDS per block of the delivery kernel.
-size_t deliver_lds_bytes();
+// The larger LDS per block of the kernels that a schedule launches.
+size_t step_lds_bytes(const StepArgs& a, int wdt, int acc_bits, int sched);
 // Periodic efficacy update of the plastic synapses after T steps.
 hipError_t launch_stdp_update(const StepArgs& a, int32_t T, hipStream_t s);
 hipError_t launch_absum_max(const unsigned long long* absum, int64_t n,

@@ -2053,7 +2053,32 @@ hipError_t launch_phase(const StepArgs& a, int wdt, int acc_bits, int phase, uin
   return hipGetLastError();
 }
 
-size_t deliver_lds_bytes() { return sizeof(DeliverLds<uint32_t, kDlvThreads, kDlvR, kDlvHash>); }
+// Update of a tile: spike ids, input sums, totals of its wavefronts.
+template <typename Acc>
+static constexpr size_t update_lds() {
+  return 1024 * 4 + 1024 * sizeof(Acc) + 4 * 4;
+}
+
+template <typename Acc, typename Ent>
+static size_t step_lds(const StepArgs& a, int sched) {
+  if (sched == DPSNN_SCHED_FUSED)
+    return std::max(2 * update_lds<Acc>(), sizeof(DeliverLds<Ent, kDlvThreads, kFusedR, kFusedHash>));
+  if (sched == DPSNN_SCHED_PERSIST)
+    return std::max(update_lds<Acc>(), sizeof(DeliverLds<Ent, 256, kPersistR, kPersistHash>));
+  const bool small = a.plastic || a.piece_len == kShortPiece || sizeof(Ent) == 8;
+  return std::max(update_lds<Acc>(),
+                  small ? sizeof(DeliverLds<Ent, kDlvThreads, kDlvRSmall, kDlvHash>)
+                        : sizeof(DeliverLds<Ent, kDlvThreads, kDlvR, kDlvHash>));
+}
+
+size_t step_lds_bytes(const StepArgs& a, int wdt, int acc_bits, int sched) {
+  const bool four = wdt != DPSNN_W_F32 || a.q_packed;
+  if (acc_bits == 32)
+    return four ? step_lds<int32_t, uint32_t>(a, sched)
+                : step_lds<int32_t, unsigned long long>(a, sched);
+  return four ? step_lds<int64_t, uint32_t>(a, sched)
+              : step_lds<int64_t, unsigned long long>(a, sched);
+}
 
 hipError_t launch_drain(const StepArgs& a, int wdt, int acc_bits, uint32_t t, hipStream_t st) {
   if (a.q_cap == 0 || a.n_tiles == 0) return hipSuccess;
