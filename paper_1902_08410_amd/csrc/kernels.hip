@@ -115,11 +115,13 @@ __host__ __device__ inline int gen_stage_bytes(int Ko) {
   return gen_pow2(Ko) * 8 + ((3 * Ko + 15) / 16) * 16 + 64 * 4;
 }
 
-// Bitonic sort of P (a power of two) keys in LDS by one wavefront, ascending.
-__device__ __forceinline__ void wave_sort(uint64_t* key, int P, int lane) {
+// Bitonic sort of P (a power of two) keys in LDS by NT threads (one wavefront,
+// or a block), ascending.
+template <int NT>
+__device__ __forceinline__ void lds_sort(uint64_t* key, int P, int tid) {
   for (int size = 2; size <= P; size <<= 1) {
     for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int q = lane; q < P / 2; q += 64) {
+      for (int q = tid; q < P / 2; q += NT) {
         const int lo = 2 * q - (q & (stride - 1));
         const int hi = lo + stride;
         const uint64_t x = key[lo], y = key[hi];
@@ -128,7 +130,10 @@ __device__ __forceinline__ void wave_sort(uint64_t* key, int P, int lane) {
           key[hi] = x;
         }
       }
-      wave_lds_sync();
+      if (NT == 64)
+        wave_lds_sync();
+      else
+        __syncthreads();
     }
   }
 }
@@ -223,7 +228,7 @@ __global__ void __launch_bounds__(256) k_gen(GenArgs a) {
   st_cnt[lane] = 0;
   wave_lds_sync();
   // the keys are distinct; the padding keys sort last
-  wave_sort(st_key, P, lane);
+  lds_sort<64>(st_key, P, lane);
   if (a.absum) {
     for (int pos = lane; pos < Ko; pos += 64)
       atomicAdd(&st_cnt[(st_key[pos] >> del_sh) & 63u], 1u);
@@ -299,26 +304,28 @@ __global__ void __launch_bounds__(256) k_gen(GenArgs a) {
   }
 }
 
-// Rows in the order they are read in, (target, delay, draw index): one
-// wavefront per row sorts the row's words in LDS (they are stored by (delay,
-// target, draw index), so equal words keep their order by place) and copies
-// the word and one value per synapse, of 1, 2 or 4 bytes.
+// Rows in the order they are read in, (target, delay, draw index): a block per
+// row sorts the row's words in LDS (they are stored by (delay, target, draw
+// index), so equal words keep their order by place) and copies the word and
+// one value per synapse, of 1, 2 or 4 bytes.  (One row of 1000 synapses read
+// back: 79 us with one wavefront a row, 45 so.)
+constexpr int kRowThreads = 256;
 template <typename T>
-__global__ void __launch_bounds__(64) k_rows(const int32_t* tgt, const T* val, int row_stride,
-                                             int Ko, int32_t* out_tgt, T* out_val) {
+__global__ void __launch_bounds__(kRowThreads) k_rows(const int32_t* tgt, const T* val,
+                                                      int row_stride, int Ko, int32_t* out_tgt,
+                                                      T* out_val) {
   extern __shared__ __align__(16) uint64_t s_key[];
-  const int lane = threadIdx.x;
   const int P = gen_pow2(Ko);
   const int64_t rb = (int64_t)blockIdx.x * row_stride, ob = (int64_t)blockIdx.x * Ko;
-  for (int j = lane; j < P; j += 64) {
+  for (int j = threadIdx.x; j < P; j += kRowThreads) {
     const int32_t w = j < Ko ? tgt[rb + j] : 0;
     s_key[j] = j < Ko ? (uint64_t)(w & kTargetMask) << 18 |
                             (uint64_t)((uint32_t)w >> kDelayShift) << 12 | (uint64_t)j
                       : ~0ull;
   }
-  wave_lds_sync();
-  wave_sort(s_key, P, lane);
-  for (int j = lane; j < Ko; j += 64) {
+  __syncthreads();
+  lds_sort<kRowThreads>(s_key, P, threadIdx.x);
+  for (int j = threadIdx.x; j < Ko; j += kRowThreads) {
     const uint64_t key = s_key[j];
     out_tgt[ob + j] = (int32_t)(key >> 18) | (int32_t)((uint32_t)(key >> 12 & 63u) << kDelayShift);
     if (val) out_val[ob + j] = val[rb + (int)(key & 4095u)];
@@ -1844,7 +1851,7 @@ hipError_t launch_gen(const GenArgs& a, int wdt, hipStream_t st) {
 hipError_t launch_rows(const int32_t* tgt, const void* val, int val_bytes, int row_stride, int Ko,
                        int64_t rows, int32_t* out_tgt, void* out_val, hipStream_t st) {
   if (rows == 0 || Ko == 0) return hipSuccess;
-  const dim3 grid((unsigned)rows), block(64);
+  const dim3 grid((unsigned)rows), block(kRowThreads);
   const size_t lds = (size_t)gen_pow2(Ko) * 8;
   if (val_bytes == 4)
     hipLaunchKernelGGL(k_rows<uint32_t>, grid, block, lds, st, tgt,
