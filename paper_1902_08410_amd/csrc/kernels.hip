@@ -1745,12 +1745,16 @@ __global__ void __launch_bounds__(256) k_persist(StepArgs a, StepOff o, uint32_t
   }
 }
 
+// A thread per tile, as far as one block goes (24x24, a step at a time with
+// the log on: 32.5 us per step with 256 threads, 29.3 with 1024).
+constexpr int kTickThreads = 1024;
+
 // Advance the device step counter after `n` steps; after a run of the fused
 // schedule (log_last) append the log of its last step first.
-__global__ void __launch_bounds__(256) k_tick(StepArgs a, uint32_t n, int log_last) {
-  __shared__ uint32_t s_w[4];
+__global__ void __launch_bounds__(kTickThreads) k_tick(StepArgs a, uint32_t n, int log_last) {
+  __shared__ uint32_t s_w[kTickThreads / 64];
   const uint32_t t1 = a.t_base[0] + n;
-  if (log_last) log_step<256>(a, t1 - 1u, 0, 1, s_w);
+  if (log_last) log_step<kTickThreads>(a, t1 - 1u, 0, 1, s_w);
   __syncthreads();  // every thread has read the counter
   if (threadIdx.x == 0) {
     // the counter and the residues the step kernels start from
@@ -1761,7 +1765,8 @@ __global__ void __launch_bounds__(256) k_tick(StepArgs a, uint32_t n, int log_la
   }
   // the emission lists of the next step start empty whatever the schedule
   if (a.emit_id)
-    for (int c = threadIdx.x; c < 2 * a.n_parts; c += 256) a.emit_n[c * kPieceStride] = 0u;
+    for (int c = threadIdx.x; c < 2 * a.n_parts; c += kTickThreads)
+      a.emit_n[c * kPieceStride] = 0u;
 }
 
 // Folds the events that are still to arrive after t steps into the slots: the
@@ -2146,7 +2151,7 @@ hipError_t launch_stdp_update(const StepArgs& a, int32_t T, hipStream_t st) {
 }
 
 hipError_t launch_tick(const StepArgs& a, uint32_t n, int sched, hipStream_t st) {
-  hipLaunchKernelGGL(k_tick, dim3(1), dim3(256), 0, st, a, n, sched == DPSNN_SCHED_FUSED ? 1 : 0);
+  hipLaunchKernelGGL(k_tick, dim3(1), dim3(kTickThreads), 0, st, a, n, sched == DPSNN_SCHED_FUSED ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -41,6 +41,22 @@ def test_runs_of_any_length_log_every_step(L, sched):
     net.close()
 
 
+def test_single_steps_of_many_tiles_are_logged(L):
+    """1030 tiles, more than the counter kernel has threads, a step at a time."""
+    p = W.tiny(w=1030, h=1, K=1024, K_out=4, nu_ext_hz=[2600.0, 2600.0], spike_log_cap=1 << 20,
+               rate_bins_cap=16)
+    print("[case] 1030 tiles", flush=True)
+    net, orc = L.dpsnn_build(p, 9), O.Oracle(p, 9, store_rows=False)
+    L.dpsnn_set_schedule(net, 0)
+    for n in (1, 1, 2, 1, 3, 1):
+        L.dpsnn_step(net, n)
+    orc.step(9)
+    st, ids = L.dpsnn_read_log(net)
+    ost, oids = orc.spikes()
+    assert len(st) > 10000 and np.array_equal(st, ost) and np.array_equal(ids, oids)
+    net.close()
+
+
 def test_a_step_of_a_short_run_costs_no_more(L):
     """5000 neurons on the default stream, nothing read between: runs of 15
     steps against runs of 20 (1.43 times the time per step with a counter
