@@ -22,6 +22,8 @@ CASES = {
     # 0.52 M neurons: few synapses per delay, or more
     "few_0.52M": (SPLIT, dict(grid_w=16, grid_h=16, K=2000, K_out=160, **J)),
     "more_0.52M": (FUSED, dict(grid_w=16, grid_h=16, K=2000, K_out=161, **J)),
+    "below_2M": (FUSED, dict(grid_w=31, grid_h=32, K=2000, K_out=161, **J)),
+    "above_2M": (SPLIT, dict(grid_w=32, grid_h=32, K=2000, K_out=161, **J)),
     "few_0.48M": (FUSED, dict(grid_w=16, grid_h=15, K=2000, K_out=160, **J)),
 }
 
