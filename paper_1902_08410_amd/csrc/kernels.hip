@@ -7,29 +7,35 @@
 //             and the start of each delay's segment.  The delay index rides
 //             in the top 6 bits of each target word.
 //  k_init     initial membrane potentials, fatigue and refractory counters.
+//  k_rows     rows back in reading order, (target, delay, draw index).
 //  k_neuron   one step of dt for a tile of 1024 neurons (4 per thread): the
 //             tile's inbox summed in LDS, the input slot read and cleared
 //             where marked, external Poisson drive, Eq. 2 update, threshold,
-//             5 ms population counts; the tile's spikes go into its history.
-//  k_deliver  the events that arrive in the next step: every block takes the
-//             spikes of a few tiles in the last d_max steps, reads from each
-//             row the segment of the delay that is due, groups the events by
-//             target tile (an LDS hash, one returning atomic per tile) and
-//             stores them in the target tiles' inboxes.  Also appends the
-//             spike log and, for plastic networks, registers the activations.
-//  k_step     fused schedule for small networks: update and delivery of the
-//             tile's own spikes in one block per tile.
+//             5 ms population counts; the tile's spikes are listed for the log
+//             and their row segments entered in the lists of their arrival
+//             steps.
+//  k_deliver  the events that arrive in the next step: blocks share the pieces
+//             of the list that is due evenly, sort their events by target tile
+//             (an LDS hash, one returning atomic per tile) and store them in
+//             the target tiles' inboxes.  Other blocks append the spike log
+//             and, for plastic networks, register the activations (without
+//             inboxes: add the events into the slots).
+//  k_step     fused schedule, one launch per step: some blocks deliver the list
+//             that is due while the others update two tiles each.
+//  k_persist  the split schedule's work for many steps in one cooperative launch.
+//  k_tick     the step counter after a run, and the log of its last fused step.
 //  k_drain    folds pending events into the slots (inspection, and before
 //             the efficacies of a plastic network change).
 //  k_stdp_update  the periodic efficacy update of plastic networks.
 //
 // Events are delivered when they arrive, not when they are emitted: rows are
-// sorted by (delay, target), each tile keeps the ids of its spikes of the
-// last d_max steps, and at step t the segment of delay d of a spike of step
-// t + 1 - d is written into the inboxes read at t + 1.  An event moves
+// sorted by (delay, target), a spike enters its row's segments, cut into
+// pieces, in the lists of the steps they arrive in, and at step t the list of
+// step t + 1 is written into the inboxes read at t + 1.  An event moves
 // once (row -> inbox -> sum) and its inbox entry needs no delay.  Events
 // that find an inbox full are added into the slot of the next step with an
-// atomic, and the (tile, slot) is marked so that the update reads that slot.
+// atomic, pieces that find a list full into the slot of their arrival, and the
+// (tile, slot) is marked so that the update reads that slot.
 // Every path sums integers, so the result does not depend on the path or
 // the order.
 //
@@ -59,14 +65,12 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Clang vector type for the non-temporal loads and stores.
+typedef float NtF4 __attribute__((ext_vector_type(4)));
+
 // Workgroup barrier that orders LDS only: global loads and stores issued
 // before it stay in flight (a full __syncthreads waits for all of them).
 // Used where threads share data through LDS alone.
-// Clang vector types for the non-temporal loads and stores.
-typedef float NtF4 __attribute__((ext_vector_type(4)));
-typedef int NtI4 __attribute__((ext_vector_type(4)));
-typedef unsigned short NtU16x4 __attribute__((ext_vector_type(4)));
-
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
@@ -1185,9 +1189,8 @@ __device__ __forceinline__ void deliver_slices(const StepArgs& a, int slot, uint
       en[r] = make_entry<Acc, WDT, PACKED>(a, c, (uint32_t)tv[r] & 1023u);
       tl[r] = (uint32_t)(tv[r] & kTargetMask) >> 10;
     }
-    // the next slice's records are on their way while this one is sorted
-    // the hashes and masks are recomputed past this point: cheaper than the
-    // registers that carrying them over takes
+    // the hashes and masks are recomputed past this point and the next such
+    // one: cheaper than the registers that carrying them over takes
     asm volatile("" : "+v"(rec_lo));
 #pragma unroll
     for (int r = 0; r < R; ++r) asm volatile("" : "+v"(tl[r]));
@@ -1200,8 +1203,6 @@ __device__ __forceinline__ void deliver_slices(const StepArgs& a, int slot, uint
       at[r] = kTabEmpty;
       if (head) at[r] = atomicCAS(&L.tab[tab_hash<HB>(tl[r])], kTabEmpty, tl[r] << 16);
     }
-    // the hashes and masks are recomputed past this point: cheaper than the
-    // registers that carrying them over takes
     asm volatile("" : "+v"(rec_lo));
 #pragma unroll
     for (int r = 0; r < R; ++r) asm volatile("" : "+v"(tl[r]));
@@ -1703,10 +1704,9 @@ __device__ __forceinline__ StepOff step_off_dev(const StepArgs& a, uint32_t t_of
 
 // Persistent schedule: n_steps steps in one cooperative launch of blocks
 // that are all resident at once (G of them).  Each step: block b updates
-// tiles b, b + G, ...; the grid synchronises; block b delivers the tile
-// groups b, b + G, ... and block 0 appends the spike log; the grid
-// synchronises.  This is the split schedule's sequence of work, so the
-// results are the same.
+// tiles b, b + G, ...; the grid synchronises; block 0 appends the spike log,
+// and all blocks share the list of pieces that is due; the grid synchronises.
+// This is the split schedule's sequence of work, so the results are the same.
 template <typename Acc, int WDT, int NP, int FMT>
 __global__ void __launch_bounds__(256) k_persist(StepArgs a, StepOff o, uint32_t n_steps) {
   __shared__ union {
