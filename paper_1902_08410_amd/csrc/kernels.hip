@@ -65,6 +65,18 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Inclusive prefix of v over the wavefront's lanes, by cross-lane moves in the
+// vector unit (rows of 16 lanes, then across the rows).
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return v;
+}
+
 // Clang vector type for the non-temporal loads and stores.
 typedef float NtF4 __attribute__((ext_vector_type(4)));
 
@@ -1130,12 +1142,7 @@ __device__ __forceinline__ void deliver_slices(const StepArgs& a, int slot, uint
       // the pieces' synapses one after the other, 64 to a row: each finds its
       // piece by its place in the wavefront's scratch
       const uint32_t n = (uint32_t)rec >> 2 & 127u;
-      uint32_t incl = n;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t x = __shfl_up(incl, off);
-        if (lane >= off) incl += x;
-      }
+      const uint32_t incl = wave_scan(n);
       T = __builtin_amdgcn_readlane((int)incl, 63);
       for (uint32_t j = 0; j < n; ++j) L.own[wave][incl - n + j] = (uint8_t)lane;
       wave_lds_sync();
@@ -1357,11 +1364,12 @@ __device__ __forceinline__ void push_pieces(const StepArgs& a, int place, int no
   for (int i0 = __builtin_amdgcn_readfirstlane((tile_tid() & 192) ^ 192); i0 < items; i0 += 256) {
     const int i = i0 + lane;
     int len = 0, slot = 0, head = 0, tail = 0;
+    int32_t s = 0;
     uint32_t pop = 0, np = 0, lost = 0;
     int64_t first = 0;
     if (i < items) {
       const int d = i / n, l = l0 + d;
-      const int32_t s = s_spk[i - d * n];
+      s = s_spk[i - d * n];
       const uint16_t* ro = a.row_off + (int64_t)s * (a.n_del + 1) + l;
       const int o0 = ro[0];
       len = (int)ro[1] - o0;
@@ -1369,26 +1377,21 @@ __device__ __forceinline__ void push_pieces(const StepArgs& a, int place, int no
       if (slot >= a.D) slot -= a.D;
       first = (int64_t)s * a.row_stride + o0;
       np = (uint32_t)(len + plen - 1) / (uint32_t)plen;
-      if (WDT == DPSNN_W_I8 && len > 0) {
-        int32_t ms;
-        int q;
-        module_pop(a, s, &ms, &q);
-        pop = (uint32_t)q;
-      }
       // first and last lane of the delay
       head = d * n - i0 > 0 ? d * n - i0 : 0;
       tail = (d + 1) * n - i0 < 64 ? (d + 1) * n - i0 - 1 : 63;
     }
-    uint32_t incl = np;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t x = __shfl_up(incl, off);
-      if (lane >= off) incl += x;
-    }
+    const uint32_t incl = wave_scan(np);
     const uint32_t before = __shfl(incl - np, head), all = __shfl(incl, tail) - before;
     const int64_t part = (int64_t)slot * a.n_parts + (place >> a.part_shift);
     uint32_t at = 0;
     if (i < items && lane == head && all) at = atomicAdd(&a.piece_n[part * kPieceStride], all);
+    if (WDT == DPSNN_W_I8 && len > 0) {
+      int32_t ms;
+      int q;
+      module_pop(a, s, &ms, &q);
+      pop = (uint32_t)q;
+    }
     at = __shfl(at, head) + incl - np - before;
     int o = 0;
     for (; o < len && at < (uint32_t)a.piece_cap; o += plen, ++at)
