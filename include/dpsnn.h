@@ -61,7 +61,7 @@ extern "C" {
 /* Step schedules (results are bit-identical; only speed differs). */
 #define DPSNN_SCHED_FUSED 0 /* one kernel per step: some blocks deliver the
                                events that are due while the others update
-                               (the default below 2 M neurons, 0.5 M for
+                               (the default below 2 M neurons, 1 M for
                                at most 8 synapses per delay, unless K_out is
                                more than 64 per delay from d_min = 1, or 256
                                without inboxes) */

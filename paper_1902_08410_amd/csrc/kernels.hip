@@ -1590,19 +1590,28 @@ __global__ void __launch_bounds__(kDlvThreads, PLAST || SHORT ? 6 : 4)
 
 // The events that arrive one step after the spikes s_spk[0 .. n) (d_min = 1:
 // the first segment of their rows), straight into the inboxes of step t + 1:
-// one wavefront per spike, one returning atomic per run of one target tile.
-template <typename Acc, int WDT, bool PACKED>
+// one returning atomic per run of one target tile; a wavefront per spike, or 16
+// lanes per spike where the segments are short (24x24 modules of 125 neurons at
+// 92 Hz, 6 synapses per delay: 18.9 us per step with a wavefront per spike, 14.8
+// so; 24x24 with 100 synapses a neuron at 95 Hz: 39.7 and 34.4).
+template <typename Acc, int WDT, bool PACKED, bool SHORT>
 __device__ __forceinline__ void deliver_first(const StepArgs& a, const StepTime& T, int n,
                                               const int32_t* s_spk) {
   typedef typename InboxEntry<Acc, WDT == DPSNN_W_F32 && !PACKED>::type Ent;
-  const int lane = threadIdx.x & 63, wave = tile_tid() >> 6;
+  constexpr int LG = SHORT ? 16 : 64, GS = 64 / LG;  // lanes per spike, spikes at a time
+  const int lane = threadIdx.x & 63, wave = tile_tid() >> 6, sub = lane & (LG - 1);
   const uint32_t par = (T.t + 1u) & 1u;
   const int slot = (int)T.slot + 1 < a.D ? (int)T.slot + 1 : 0;
   uint32_t* in_cnt = a.in_cnt + (int64_t)par * a.n_tiles * kInboxStride;
   Ent* in_q = static_cast<Ent*>(a.in_q) + (int64_t)par * a.n_tiles * a.in_stride;
-  for (int k = wave; k < n; k += 4) {
-    const int32_t s = __builtin_amdgcn_readfirstlane(s_spk[k]);
-    const int end = __builtin_amdgcn_readfirstlane((int)a.row_off[(int64_t)s * (a.n_del + 1) + 1]);
+  for (int k0 = wave * GS; k0 < n; k0 += 4 * GS) {
+    const int k = k0 + lane / LG;
+    int32_t s = s_spk[k < n ? k : n - 1];
+    int end = k < n ? (int)a.row_off[(int64_t)s * (a.n_del + 1) + 1] : 0;
+    if (!SHORT) {
+      s = __builtin_amdgcn_readfirstlane(s);
+      end = __builtin_amdgcn_readfirstlane(end);
+    }
     uint32_t pop = 0;
     if (WDT == DPSNN_W_I8) {
       int32_t ms;
@@ -1611,25 +1620,28 @@ __device__ __forceinline__ void deliver_first(const StepArgs& a, const StepTime&
       pop = (uint32_t)q << 8;
     }
     const int64_t rb = (int64_t)s * a.row_stride;
-    for (int o = 0; o < end; o += 64) {
-      const int m = end - o < 64 ? end - o : 64;
-      const int64_t x = rb + o + (lane < m ? lane : m - 1);
+    for (int o = 0; SHORT ? (bool)__any(o < end) : o < end; o += LG) {
+      const int left = end - o < 0 ? 0 : end - o, m = left < LG ? left : LG;
+      // (lanes past the segment read its last synapse, or the row's first)
+      const int64_t x = m ? rb + o + (sub < m ? sub : m - 1) : rb;
       const int32_t target = a.tgt[x] & kTargetMask;
       const Ent e = make_entry<Acc, WDT, PACKED>(a, load_code<WDT>(a, x, 0u) | pop,
                                                  (uint32_t)target & 1023u);
       const int tl = target >> 10;
       const int prev = __builtin_amdgcn_update_dpp(-1, tl, 0x138, 0xf, 0xf, false);
-      const bool head = lane < m && prev != tl;
+      const bool head = sub < m && (prev != tl || (SHORT && sub == 0));
       const unsigned long long heads = __ballot(head);
       const unsigned long long after = heads >> lane >> 1;
+      // the run ends with the segment or at the next head
+      const int to_head = after ? __ffsll(after) : 64, to_end = m - sub;
       uint32_t v = 0;
       if (head)
         v = atomicAdd(&in_cnt[(int64_t)tl * kInboxStride],
-                      (uint32_t)(after ? __ffsll(after) : m - lane)) -
+                      (uint32_t)(to_head < to_end ? to_head : to_end)) -
             (uint32_t)lane;
       const unsigned long long upto = heads & ((2ull << lane) - 1ull);
-      const uint32_t pos = __shfl(v, 63 - __clzll((long long)upto)) + (uint32_t)lane;
-      if (lane < m) {
+      const uint32_t pos = __shfl(v, upto ? 63 - __clzll((long long)upto) : 0) + (uint32_t)lane;
+      if (sub < m) {
         if (pos < (uint32_t)a.in_cap)
           in_q[(int64_t)tl * a.in_stride + pos] = e;
         else
@@ -1685,7 +1697,7 @@ __global__ void __launch_bounds__(kDlvThreads, 6) k_step(StepArgs a, StepOff o, 
   if (n == 0) return;
   if (a.q_cap) {
     push_pieces<Acc, WDT>(a, a.tile_place[tile], (int)T.slot, a.d_min == 1 ? 1 : 0, n, spk);
-    if (a.d_min == 1) deliver_first<Acc, WDT, PACKED>(a, T, n, spk);
+    if (a.d_min == 1) deliver_first<Acc, WDT, PACKED, SHORT>(a, T, n, spk);
   } else {
     for (int k = tid >> 6; k < n; k += 4) {
       const int32_t id = __builtin_amdgcn_readfirstlane(spk[k]);

@@ -19,12 +19,12 @@ CASES = {
     # no inboxes: by request, or for more than 128 slots
     "no_inboxes": (SPLIT, dict(queue_cap=-1)), "slots_150": (SPLIT, dict(d_min=100, d_max=149)),
     "no_inboxes_256": (FUSED, dict(queue_cap=-1, K_out=256)),
-    # 0.52 M neurons: few synapses per delay, or more
-    "few_0.52M": (SPLIT, dict(grid_w=16, grid_h=16, K=2000, K_out=160, **J)),
-    "more_0.52M": (FUSED, dict(grid_w=16, grid_h=16, K=2000, K_out=161, **J)),
+    # 1.02 M neurons: few synapses per delay, or more
+    "few_1.02M": (SPLIT, dict(grid_w=16, grid_h=32, K=2000, K_out=160, **J)),
+    "more_1.02M": (FUSED, dict(grid_w=16, grid_h=32, K=2000, K_out=161, **J)),
     "below_2M": (FUSED, dict(grid_w=31, grid_h=32, K=2000, K_out=161, **J)),
     "above_2M": (SPLIT, dict(grid_w=32, grid_h=32, K=2000, K_out=161, **J)),
-    "few_0.48M": (FUSED, dict(grid_w=16, grid_h=15, K=2000, K_out=160, **J)),
+    "few_0.99M": (FUSED, dict(grid_w=16, grid_h=31, K=2000, K_out=160, **J)),
 }
 
 

@@ -52,6 +52,14 @@ CASES = {
     "segment_8_f16": _tiny(K_out=8, weight_dtype="f16", **_AT2),
     "segment_9_i8": _tiny(K_out=9, weight_dtype="i8", **_AT2),
     "segment_17_wide64": _tiny(K_out=17, acc_bits=64, q_frac_bits=32, **_AT2),
+    # the fused schedule's own delivery of the first delay: 15 to 17 synapses, four
+    # spikes at a time, many spikes a tile and few
+    "segment_15_d1": _tiny(K_out=15, d_min=1, d_max=1),
+    "segment_16_d1_f16": _tiny(K_out=16, weight_dtype="f16", d_min=1, d_max=1),
+    "segment_17_d1_i8": _tiny(K_out=17, weight_dtype="i8", d_min=1, d_max=1),
+    "bursts_16_d1": W.tiny(K_out=16, d_min=1, d_max=1, **_HARD),
+    "few_spikes_d1": _tiny(K_out=18, d_min=1, d_max=1, nu_ext_hz=[1500.0, 1500.0]),
+    "inbox_full_d1": _tiny(K_out=18, queue_cap=3, d_min=1, d_max=1),
     "segment_20_d1": _tiny(K_out=20, d_min=1, d_max=1),
     "segment_21_d1": _tiny(K_out=21, d_min=1, d_max=1),
     "line_short": _tiny(K_out=100, d_max=5), "line_long": _tiny(K_out=101, d_max=5),
