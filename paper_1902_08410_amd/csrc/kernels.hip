@@ -118,6 +118,15 @@ __device__ __forceinline__ void module_pop(const StepArgs& a, int32_t id, int32_
   *pop = (l >= nd.pop_hi[0]) + (l >= nd.pop_hi[1]) + (l >= nd.pop_hi[2]);
 }
 
+// Population of neuron id of tile `tile` (uniform: its network's constants come
+// by scalar loads).
+__device__ __forceinline__ uint32_t pop_in_tile(const StepArgs& a, int tile, int32_t id) {
+  const NetDev& nd = a.nets[__builtin_amdgcn_readfirstlane(a.tile_net[tile])];
+  const uint32_t local = (uint32_t)(id - (int32_t)nd.base);
+  const int32_t l = (int32_t)(local - module_of(nd, local) * (uint32_t)nd.K);
+  return (uint32_t)((l >= nd.pop_hi[0]) + (l >= nd.pop_hi[1]) + (l >= nd.pop_hi[2]));
+}
+
 // ------------------------------------------------------------------------
 // Connectivity generation
 __host__ __device__ inline int gen_pow2(int Ko) {
@@ -1343,9 +1352,9 @@ __device__ __forceinline__ void deliver_slices(const StepArgs& a, int slot, uint
   }
 }
 
-// Enters the spikes s_spk[0 .. n) of the tile at place `place` (slot `now` =
-// t mod D) in the lists of their arrival steps, delays of index l0 and more;
-// by the tile's threads.  Pieces that find a list full go into the slots, a
+// Enters the spikes s_spk[0 .. n) of tile `tile` (slot `now` = t mod D) in the
+// lists of their arrival steps, delays of index l0 and more; by the tile's
+// threads.  Pieces that find a list full go into the slots, a
 // wavefront per piece (48x48 with a single delay, 16 pieces a spike, 7 % of the
 // neurons in the largest step: update 1341 us when lists held a piece per
 // neuron and the lane that found one full added its synapses alone, 64 now).
@@ -1355,8 +1364,9 @@ __device__ __forceinline__ void deliver_slices(const StepArgs& a, int slot, uint
 // delay give every pair its place (48x48: update 30.1 us with an atomic per
 // pair, 28.7 so; with 100 synapses a neuron and 96 Hz 70 and 36).
 template <typename Acc, int WDT>
-__device__ __forceinline__ void push_pieces(const StepArgs& a, int place, int now, int l0, int n,
+__device__ __forceinline__ void push_pieces(const StepArgs& a, int tile, int now, int l0, int n,
                                             const int32_t* s_spk) {
+  const int place = a.tile_place[tile];
   const int nl = a.n_del - l0, lane = threadIdx.x & 63, items = n * nl;
   const int plen = a.piece_len;
   // (from the last wavefront on: the first ones deliver the events of delay 1
@@ -1386,12 +1396,7 @@ __device__ __forceinline__ void push_pieces(const StepArgs& a, int place, int no
     const int64_t part = (int64_t)slot * a.n_parts + (place >> a.part_shift);
     uint32_t at = 0;
     if (i < items && lane == head && all) at = atomicAdd(&a.piece_n[part * kPieceStride], all);
-    if (WDT == DPSNN_W_I8 && len > 0) {
-      int32_t ms;
-      int q;
-      module_pop(a, s, &ms, &q);
-      pop = (uint32_t)q;
-    }
+    if (WDT == DPSNN_W_I8) pop = pop_in_tile(a, tile, s);
     at = __shfl(at, head) + incl - np - before;
     int o = 0;
     for (; o < len && at < (uint32_t)a.piece_cap; o += plen, ++at)
@@ -1537,7 +1542,7 @@ __device__ __forceinline__ void list_spikes(const StepArgs& a, const StepTime& T
     int32_t* out = a.emit_id + ((int64_t)part << (a.part_shift + 10)) + s_wt[0];
     for (int k = tid; k < n; k += 256) out[k] = s_spk[k];
   }
-  if (a.q_cap) push_pieces<Acc, WDT>(a, a.tile_place[tile], (int)T.slot, 0, n, s_spk);
+  if (a.q_cap) push_pieces<Acc, WDT>(a, tile, (int)T.slot, 0, n, s_spk);
 }
 
 template <typename Acc, int NP, int FMT, int WDT>
@@ -1595,8 +1600,8 @@ __global__ void __launch_bounds__(kDlvThreads, PLAST || SHORT ? 6 : 4)
 // 92 Hz, 6 synapses per delay: 18.9 us per step with a wavefront per spike, 14.8
 // so; 24x24 with 100 synapses a neuron at 95 Hz: 39.7 and 34.4).
 template <typename Acc, int WDT, bool PACKED, bool SHORT>
-__device__ __forceinline__ void deliver_first(const StepArgs& a, const StepTime& T, int n,
-                                              const int32_t* s_spk) {
+__device__ __forceinline__ void deliver_first(const StepArgs& a, const StepTime& T, int tile,
+                                              int n, const int32_t* s_spk) {
   typedef typename InboxEntry<Acc, WDT == DPSNN_W_F32 && !PACKED>::type Ent;
   constexpr int LG = SHORT ? 16 : 64, GS = 64 / LG;  // lanes per spike, spikes at a time
   const int lane = threadIdx.x & 63, wave = tile_tid() >> 6, sub = lane & (LG - 1);
@@ -1612,13 +1617,7 @@ __device__ __forceinline__ void deliver_first(const StepArgs& a, const StepTime&
       s = __builtin_amdgcn_readfirstlane(s);
       end = __builtin_amdgcn_readfirstlane(end);
     }
-    uint32_t pop = 0;
-    if (WDT == DPSNN_W_I8) {
-      int32_t ms;
-      int q;
-      module_pop(a, s, &ms, &q);
-      pop = (uint32_t)q << 8;
-    }
+    const uint32_t pop = WDT == DPSNN_W_I8 ? pop_in_tile(a, tile, s) << 8 : 0u;
     const int64_t rb = (int64_t)s * a.row_stride;
     for (int o = 0; SHORT ? (bool)__any(o < end) : o < end; o += LG) {
       const int left = end - o < 0 ? 0 : end - o, m = left < LG ? left : LG;
@@ -1696,8 +1695,8 @@ __global__ void __launch_bounds__(kDlvThreads, 6) k_step(StepArgs a, StepOff o, 
   list_for_log(a, T, tile, n, spk);
   if (n == 0) return;
   if (a.q_cap) {
-    push_pieces<Acc, WDT>(a, a.tile_place[tile], (int)T.slot, a.d_min == 1 ? 1 : 0, n, spk);
-    if (a.d_min == 1) deliver_first<Acc, WDT, PACKED, SHORT>(a, T, n, spk);
+    push_pieces<Acc, WDT>(a, tile, (int)T.slot, a.d_min == 1 ? 1 : 0, n, spk);
+    if (a.d_min == 1) deliver_first<Acc, WDT, PACKED, SHORT>(a, T, tile, n, spk);
   } else {
     for (int k = tid >> 6; k < n; k += 4) {
       const int32_t id = __builtin_amdgcn_readfirstlane(spk[k]);
